@@ -102,11 +102,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 3 && SH
 #pragma unroll
     for (int l = 0; l < D; ++l) x[l] = a.x[l][i];
   };
-  // a position that is not finite takes the cell of the origin, as a valid node
   auto locate = [&](int64_t i, double* f) __attribute__((always_inline)) {
     double x[D];
     position(i, x);
-    return max(base_cell<D, SH>(M, x, f), 0);
+    return base_cell<D, SH>(M, x, f);
   };
   // v = V(p) of particle i and its deposit weights q/dV (1, v)
   auto velocity = [&](int64_t i, double* coef) __attribute__((always_inline)) {

@@ -12,6 +12,7 @@
 #include <limits.h>
 #include <stdint.h>
 
+#include "cell.h"
 #include "gmhc_internal.h"
 
 namespace gmhc {
@@ -147,21 +148,16 @@ struct Batches {
   }
 };
 
-// Base cell of a position (linear index, -1 where it is not finite or far off) and the
-// offset from its base node.
-template <int D, int SH, class R>
-__device__ __forceinline__ int base_cell(const Mesh& M, const double* x, R* f0) {
-  bool ok = true;
+// Base cell of a position (linear index) and the offset from its base node.
+template <int D, int SH>
+__device__ __forceinline__ int base_cell(const Mesh& M, const double* x, double* f0) {
   int cell = 0;
 #pragma unroll
   for (int l = 0; l < D; ++l) {
-    const double xi = (x[l] - M.lo[l]) * M.inv_h[l];
-    ok = ok && fabs(xi) < 1.0e8;  // false for a NaN
-    const double jr = ok ? floor(SH == 2 ? xi + 0.5 : xi) : 0.0;
-    f0[l] = ok ? (R)(xi - jr) : R(0);
-    cell |= ((int)jr & (M.n[l] - 1)) << (l == 0 ? 0 : (l == 1 ? M.ln[0] : M.ln[0] + M.ln[1]));
+    const int j = (int)axis_node(M, l, SH == 1, x[l], f0[l]);
+    cell |= (j & (M.n[l] - 1)) << (l == 0 ? 0 : (l == 1 ? M.ln[0] : M.ln[0] + M.ln[1]));
   }
-  return ok ? cell : -1;
+  return cell;
 }
 
 // Mesh index of the node at offset (k0, k1, k2) from the base node of a cell.

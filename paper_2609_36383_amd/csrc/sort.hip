@@ -18,6 +18,7 @@
 
 #include <algorithm>
 
+#include "cell.h"
 #include "gmhc_internal.h"
 
 namespace gmhc {
@@ -318,19 +319,17 @@ __global__ __launch_bounds__(kBlock) void k_gather(SortArgs a, const int32_t* pe
   a.id_dst[i] = a.id_src[k];
 }
 
-// Base cell of every particle (the nearest node for S_2, the node below for S_1).
+// Base cell of every particle.
 __global__ __launch_bounds__(kBlock) void k_cell_plain(SortArgs a) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.np) return;
-  int64_t mul = 1, gg = 0;
+  int cell = 0, shift = 0;
   for (int l = 0; l < a.M.d; ++l) {
-    const double xi = (a.x[l][i] - a.M.lo[l]) * a.M.inv_h[l];
-    double r = floor(a.M.shape == 1 ? xi : xi + 0.5);
-    if (!(r > -1.0e9 && r < 1.0e9)) r = 0.0;
-    gg += (int64_t)wrapi((int)r, a.M.n[l]) * mul;
-    mul *= a.M.n[l];
+    double f;
+    cell |= ((int)axis_node(a.M, l, a.M.shape == 1, a.x[l][i], f) & (a.M.n[l] - 1)) << shift;
+    shift += a.M.ln[l];
   }
-  a.key[i] = (int32_t)gg;
+  a.key[i] = cell;
 }
 
 int key_bits(int64_t Ng) {
