@@ -118,7 +118,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 3 && SH
     for (int c = 0; c < 3; ++c) {
       const double v = p[c] / (m * g);
       st_bulk(a.v[c], i, v, a.prec);
-      coef[1 + c] = coef[0] * v;
+      // a velocity that is not finite (a bad momentum, no charge) deposits nothing: its row's
+      // sums are the neighbours' too
+      coef[1 + c] = isfinite(v) ? coef[0] * v : 0.0;
     }
   };
   // what the potential at particle i is gathered for

@@ -1,8 +1,9 @@
-"""A particle with a bad position among good ones at initialization.  Positions are not checked
+"""A bad particle among good ones at initialization.  Positions are not checked
 at load; the passes over particles at one time take a coordinate that is not finite (or 1e9
 cells away) as the origin's on that axis, whatever the particle's place in its batch, and leave
-the other particles as they are.  The reference is the oracle's run with the coordinate put
-there.
+the other particles as they are.  A particle whose velocity is not finite (a momentum that is
+not, or no charge) deposits no current.  The reference is the oracle's run with the coordinate
+put there, or with the particle at rest.
 
 Tolerances as in test_gpu_point_passes.py: 1e-13 for momenta, 1e-11 for sums."""
 import numpy as np
@@ -62,4 +63,28 @@ def test_bad_position(dim, shape, bad):
     sim.close()
     err = [_rel(Pg, Po), _rel(vg, vo)] + [_rel(fg[f], fo[f]) for f in ("rho", "J")]
     _say(f"d={dim} S{shape} {bad} particle {b} of {num}: P {err[0]:.1e} v {err[1]:.1e} rho {err[2]:.1e} J {err[3]:.1e}")
+    assert max(err[:2]) < 1e-13 and max(err[2:]) < 1e-11
+
+
+@pytest.mark.parametrize("dim", [1, 2, 3])
+@pytest.mark.parametrize("shape", [2, 1])
+@pytest.mark.parametrize("bad", ["momentum_nan", "momentum_inf", "no_charge"])
+def test_velocity_not_finite(dim, shape, bad):
+    G = _gpu()
+    num = 20 * int(np.prod(N[dim])) + 7
+    n, length, x, u, q, b = _inputs(dim, num, 70 + dim, N[dim][0] // 2)
+    _, A0, U0, _ = W.random_fields(dim, n, length, seed=80 + dim, amp=0.2)
+    ug, uo, qg, qo = u.copy(), u.copy(), q.copy(), q.copy()
+    uo[:, b] = 0.0
+    if bad == "no_charge":
+        qg[b], qo[b] = 0.0, 1e-40
+    else:
+        ug[1, b] = np.nan if bad == "momentum_nan" else np.inf
+    kw = dict(dim=dim, n=n, lo=(0.0,) * dim, length=length, dt=0.05, shape_order=shape)
+    _, (_, Po, vo), fo = _state(O.OracleSim, O.make_config(**kw, gl_order=8), x, uo, qo, A0, U0)
+    sim, (_, Pg, vg), fg = _state(G.Simulation, G.make_config(**kw), x, ug, qg, A0, U0)
+    sim.close()
+    good = np.arange(num) != b
+    err = [_rel(Pg[:, good], Po[:, good]), _rel(vg[:, good], vo[:, good])] + [_rel(fg[f], fo[f]) for f in ("rho", "J")]
+    _say(f"d={dim} S{shape} {bad}: P {err[0]:.1e} v {err[1]:.1e} rho {err[2]:.1e} J {err[3]:.1e}")
     assert max(err[:2]) < 1e-13 and max(err[2:]) < 1e-11
