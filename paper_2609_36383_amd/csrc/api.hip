@@ -804,7 +804,7 @@ int32_t gmhc_initialize(gmhc_ctx* ctx) {
   ia.q = ctx->q;
   ia.prec = ctx->prec;
   ia.rho = rho_fx;
-  HIPCK(cell_order(sort_args(ctx), &ia.keys, &ia.perm, s));
+  if (point_order_pays(ctx->np, Ng)) HIPCK(cell_order(sort_args(ctx), &ia.keys, &ia.perm, s));
   HIPCK(launch_init_deposit(ia, s));
   HIPCK(launch_fix_to_double(rho_fx, ctx->rscr, Ng, M.fx, s));
   HIPCK(launch_fix_to_double(ctx->Jdep, ctx->rscr + Ng, 3 * Ng, M.fx, s));

@@ -276,7 +276,7 @@ struct InitArgs {
   void* P[3];            // in: mechanical p; out: unchanged (canonical pass adds q A)
   const void* q;
   void* v[3];            // out: V(p)
-  const int32_t* keys;   // the particles' order by cell (cell_order)
+  const int32_t* keys;   // the particles' order by cell (cell_order), or null: storage order
   const int32_t* perm;
   unsigned long long* rho;  // [Ng] fixed-point accumulator pairs
   unsigned long long* J;    // [3][Ng] fixed-point accumulator pairs
@@ -307,7 +307,7 @@ struct CanonArgs {
   void* P[3];
   const void* q;
   const double* A[3];    // real A^0, components Ng apart
-  const int32_t* keys;   // the particles' order by cell (cell_order)
+  const int32_t* keys;   // the particles' order by cell (cell_order), or null: storage order
   const int32_t* perm;
   double sign;           // +1: P = p + q A ; -1: p = P - q A
 };
@@ -328,6 +328,15 @@ struct KinArgs {
 // partials of launch_kinetic.
 constexpr int kPointBlocks = 8192;
 int point_blocks(int64_t np);
+// Whether initialization takes the particles in their order by cell: the index sort's dozen
+// launches cost 50 to 70 us, and its batches need a few particles per cell.  Measured run starts,
+// in random order, with the sort and without: 1024 cells in 1D, 16,384 particles 168 and 120 us,
+// 65,536 173 and 184 us, 131,072 183 and 279 us; 128^2, 65,536 (four per cell) 315 and 332 us
+// (linear shape 250 and 206 us), 131,072 (eight) 239 and 547 us; 32^3, 131,072 (four) 946 and
+// 1428 us, 262,144 (eight) 485 and 2721 us.
+inline bool point_order_pays(int64_t np, int64_t Ng) {
+  return np >= 65536 && np >= (np < 131072 ? 8 : 4) * Ng;
+}
 hipError_t launch_kinetic(const KinArgs& a, hipStream_t s);
 
 struct SpecDiagArgs {

@@ -8,10 +8,10 @@
 // batch of particles of one cell: the deposit is summed over the batch, and over the row's
 // following batches of the same cell, as moments before a node is touched, and the gather
 // reads the cell's three polynomials once per row and broadcasts their coefficients.  At
-// initialization the particles may be in any order, so they are taken through their stable
-// order by cell (an index sort; the storage order stays).  Elsewhere the storage order serves,
-// and a window whose particles are too scattered (fewer than four per batch on average) takes
-// the thread-per-particle path.
+// initialization the particles may be in any order, so where it pays (point_order_pays) they are
+// taken through their stable order by cell (an index sort; the storage order stays).  Elsewhere
+// the storage order serves, and a window whose particles are too scattered (fewer than four per
+// batch on average) takes one particle per lane.
 //
 // Measured at 8,388,608 particles on 64^3 (32 per cell, in grid-cell order): the deposit 76.2
 // to 0.80 ms (the index sort adds 0.3 ms), the canonical momenta 1.74 to 0.59 ms, the kinetic
@@ -29,12 +29,13 @@
 namespace gmhc {
 namespace {
 
-constexpr int kPointWindow = 256;   // particles per listing of batches
-constexpr int kPointBatches = 64;   // batches of a window, at most, for the row path
+constexpr int kPointWindow = 256;  // particles per listing of batches, at most
+constexpr int kPointBatch = 4;     // particles per batch of a window, on average and at least, for the row path
+constexpr int kPointFill = 2048;   // workgroups that fill the chip (two waves per SIMD)
 
 struct PointArgs {
   Mesh M;
-  int64_t np, per;  // particles, and particles per workgroup (a multiple of the window)
+  int64_t np, per;  // particles, and particles per workgroup
   double kappa, sign;
   int prec;
   const double* x[3];
@@ -68,13 +69,15 @@ __device__ __forceinline__ void each_node(const Mesh& M, int cell, const double*
       w[l][2] = 0.5 * b * b;
     }
   }
+  // a row of nodes along x at a time, so that its reads are in flight together
 #pragma unroll 1
-  for (int p = 0; p < NP; ++p) {
-    const int i = p % N, j = (p / N) % N, k = p / (N * N);
-    double s = i == 0 ? w[0][0] : (i == 1 ? w[0][1] : w[0][N - 1]);
+  for (int r = 0; r < NP / N; ++r) {
+    const int j = r % N, k = r / N;
+    double s = 1.0;
     if constexpr (D > 1) s *= j == 0 ? w[1][0] : (j == 1 ? w[1][1] : w[1][N - 1]);
     if constexpr (D > 2) s *= k == 0 ? w[2][0] : (k == 1 ? w[2][1] : w[2][N - 1]);
-    fn(cell_node<D>(M, cell, i - off, j - off, k - off), s);
+#pragma unroll
+    for (int i = 0; i < N; ++i) fn(cell_node<D>(M, cell, i - off, j - off, k - off), s * w[0][i]);
   }
 }
 
@@ -174,7 +177,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 3 && SH
       double f[D];
       return locate(w0 + r, f);
     });
-    if (bt.nb > kPointBatches) {  // scattered particles: one per lane
+    if (kPointBatch * bt.nb > wn) {  // scattered particles: one per lane
 #pragma unroll 1
       for (int r = lane; r < wn; r += 64) {
         const int64_t i = a.perm ? a.perm[w0 + r] : w0 + r;
@@ -247,11 +250,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 3 && SH
   }
 }
 
-// Workgroups of a pass: eight waves per SIMD's worth at most, whole windows each.
+// Particles per workgroup: one window, shorter (down to a wave's lanes) while the workgroups are
+// too few to fill the chip, and several windows beyond eight waves per SIMD's worth of workgroups.
+// With whole windows throughout, the kinetic energy's read-out took 5 to 10 us more for up to
+// 131,072 particles (3D, 1,000 particles: 49 against 29 us).
 int64_t point_per(int64_t np) {
+  const int64_t waves = (np + 63) / 64;
+  if (waves <= kPointFill * (kPointWindow / 64)) return 64 * std::max<int64_t>((waves + kPointFill - 1) / kPointFill, 1);
   const int64_t windows = (np + kPointWindow - 1) / kPointWindow;
-  const int64_t per = std::max<int64_t>((windows + kPointBlocks - 1) / kPointBlocks, 1);
-  return per * kPointWindow;
+  return kPointWindow * ((windows + kPointBlocks - 1) / kPointBlocks);
 }
 
 template <int MODE>

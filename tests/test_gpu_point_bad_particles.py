@@ -5,7 +5,7 @@ the other particles as they are.  A particle whose velocity is not finite (a mom
 not, or no charge) deposits no current.  The reference is the oracle's run with the coordinate
 put there, or with the particle at rest.
 
-Tolerances as in test_gpu_point_passes.py: 1e-13 for momenta, 1e-11 for sums."""
+Tolerances as in test_gpu_point_passes.py: 1e-13 for momenta, N eps for sums, 1.5e-11 at these N."""
 import numpy as np
 import pytest
 
@@ -43,10 +43,10 @@ def _state(cls, cfg, x, u, q, A0, U0):
 
 @pytest.mark.parametrize("dim", [1, 2, 3])
 @pytest.mark.parametrize("shape", [2, 1])
+@pytest.mark.parametrize("num", [1543, 65543])  # in storage order, and in the order by cell
 @pytest.mark.parametrize("bad", ["nan", "inf", "far", "cells_away"])
-def test_bad_position(dim, shape, bad):
+def test_bad_position(dim, shape, num, bad):
     G = _gpu()
-    num = 20 * int(np.prod(N[dim])) + 7
     # its cell as the passes take it: column 0, or its own
     n, length, x, u, q, b = _inputs(dim, num, 50 + dim, N[dim][0] // 2 if bad == "cells_away" else 0)
     _, A0, U0, _ = W.random_fields(dim, n, length, seed=60 + dim, amp=0.2)
@@ -63,15 +63,15 @@ def test_bad_position(dim, shape, bad):
     sim.close()
     err = [_rel(Pg, Po), _rel(vg, vo)] + [_rel(fg[f], fo[f]) for f in ("rho", "J")]
     _say(f"d={dim} S{shape} {bad} particle {b} of {num}: P {err[0]:.1e} v {err[1]:.1e} rho {err[2]:.1e} J {err[3]:.1e}")
-    assert max(err[:2]) < 1e-13 and max(err[2:]) < 1e-11
+    assert max(err[:2]) < 1e-13 and max(err[2:]) < 1.5e-11
 
 
 @pytest.mark.parametrize("dim", [1, 2, 3])
 @pytest.mark.parametrize("shape", [2, 1])
+@pytest.mark.parametrize("num", [1543, 65543])
 @pytest.mark.parametrize("bad", ["momentum_nan", "momentum_inf", "no_charge"])
-def test_velocity_not_finite(dim, shape, bad):
+def test_velocity_not_finite(dim, shape, num, bad):
     G = _gpu()
-    num = 20 * int(np.prod(N[dim])) + 7
     n, length, x, u, q, b = _inputs(dim, num, 70 + dim, N[dim][0] // 2)
     _, A0, U0, _ = W.random_fields(dim, n, length, seed=80 + dim, amp=0.2)
     ug, uo, qg, qo = u.copy(), u.copy(), q.copy(), q.copy()
@@ -86,5 +86,5 @@ def test_velocity_not_finite(dim, shape, bad):
     sim.close()
     good = np.arange(num) != b
     err = [_rel(Pg[:, good], Po[:, good]), _rel(vg[:, good], vo[:, good])] + [_rel(fg[f], fo[f]) for f in ("rho", "J")]
-    _say(f"d={dim} S{shape} {bad}: P {err[0]:.1e} v {err[1]:.1e} rho {err[2]:.1e} J {err[3]:.1e}")
-    assert max(err[:2]) < 1e-13 and max(err[2:]) < 1e-11
+    _say(f"d={dim} S{shape} {bad} of {num}: P {err[0]:.1e} v {err[1]:.1e} rho {err[2]:.1e} J {err[3]:.1e}")
+    assert max(err[:2]) < 1e-13 and max(err[2:]) < 1.5e-11
