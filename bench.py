@@ -237,6 +237,9 @@ def run_case(args, w, fp32, parts, tol_of_fp32=None):
     ng = int(np.prod(w["n"]))
     seg_mean = segs / max(evals, 1)  # measured knot-split segments per evaluation
     # flops of the timed launches (evaluations per launch of the timed steps)
+    # the kernel's quadrature: closed form (-1), points of the least exact order, or the run's points (0)
+    exact = d + 1 if sh == 2 else (d + 2) // 2
+    quad = 0 if ngl < exact else (exact if fp32 else -1)
     flops_launch = (timed_evals / max(timed_launches, 1)) * flops_per_eval(d, seg_mean, ngl, sh)
     bytes_launch = npart * bytes_per_particle(d, 4 if fp32 else 8) + ng * bytes_per_node(d)
     launch_s = (orbit_ms / max(timed_launches, 1)) * 1e-3
@@ -254,8 +257,7 @@ def run_case(args, w, fp32, parts, tol_of_fp32=None):
             "bound": "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
             "traffic": measured_traffic(args.workload, "fp32" if fp32 else "fp64", sh),
             "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE x2.0 + WRITE_SIZE x1.0)",
-            "kernel": f"k_orbit<{d}, {sh}, {'true' if ngl >= (d + 1 if sh == 2 else (d + 2) // 2) else 'false'}, "
-                      f"{'float' if fp32 else 'double'}, false>", "launch_ms": launch_s * 1e3,
+            "kernel": f"k_orbit<{d}, {sh}, {quad}, {'float' if fp32 else 'double'}, false>", "launch_ms": launch_s * 1e3,
             "flops_per_launch": flops_launch, "hbm_bytes_per_launch": bytes_launch,
             "hbm_achieved_gbs": gbs, "hbm_frac": gbs / PEAK_HBM_GBS,
             # the published FP32 peak counts packed instructions, which this build does not

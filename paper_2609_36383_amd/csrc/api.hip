@@ -21,8 +21,10 @@ static_assert(kMaxRefine == 3, "gmhc_config.refine_levels is documented as 0..3"
 struct gmhc_ctx {
   gmhc_config cfg;
   Mesh M;
-  int ngl = 0;
+  int ngl = 0;  // Gauss-Legendre points of a segment as configured
   double glx[kMaxGL], glw[kMaxGL];
+  int ongl = 0;  // the orbit pass's: no more than the least exact rule's
+  double oglx[kMaxGL], oglw[kMaxGL];
   int64_t np = 0;
   hipStream_t stream = nullptr;
   int device = 0;
@@ -307,10 +309,10 @@ OrbitArgs orbit_args(gmhc_ctx* c, int iterate, int par = 0) {
   a.max_inner = c->cfg.max_inner;
   a.iterate = iterate;
   a.deposit = 1;
-  a.ngl = c->ngl;
+  a.ngl = c->ongl;
   for (int k = 0; k < kMaxGL; ++k) {
-    a.glx[k] = c->glx[k];
-    a.glw[k] = c->glw[k];
+    a.glx[k] = c->oglx[k];
+    a.glw[k] = c->oglw[k];
   }
   a.ps = std::max<int64_t>(c->np, 1);
   a.precision = c->cfg.precision;
@@ -601,7 +603,7 @@ void set_geometry(const gmhc_config& c, Mesh& M, int& ngl, double* glx, double* 
     M.Ng *= M.n[l];
     if (r) M.dV *= M.h[l];
   }
-  ngl = c.gl_order ? c.gl_order : (M.shape == 1 ? (c.dim + 2) / 2 : c.dim + 1);
+  ngl = c.gl_order ? c.gl_order : exact_order(M);
   for (int k = 0; k < kMaxGL; ++k) glx[k] = glw[k] = 0.0;
   gl01(ngl, glx, glw);
 }
@@ -636,6 +638,9 @@ int32_t gmhc_create(const gmhc_config* cfg, gmhc_ctx** out) {
   ctx->prec = cfg->precision;
   ctx->es = cfg->precision == GMHC_FP32_BULK ? sizeof(float) : sizeof(double);
   set_geometry(*cfg, ctx->M, ctx->ngl, ctx->glx, ctx->glw);
+  ctx->ongl = std::min(ctx->ngl, exact_order(ctx->M));
+  for (int k = 0; k < kMaxGL; ++k) ctx->oglx[k] = ctx->oglw[k] = 0.0;
+  gl01(ctx->ongl, ctx->oglx, ctx->oglw);
   *out = ctx;
   return GMHC_OK;
 }

@@ -381,6 +381,9 @@ bool config_ok(const gmhc_config& c);
 // Mesh geometry and the Gauss-Legendre rule (nodes and weights on [0, 1], kMaxGL slots)
 // of a valid configuration.
 void set_geometry(const gmhc_config& c, Mesh& M, int& ngl, double* glx, double* glw);
+// The least Gauss-Legendre order that is exact on a knot segment: the integrands are polynomials
+// of degree 2 d (S_2) or d (S_1) there.
+inline int exact_order(const Mesh& M) { return M.shape == 1 ? (M.d + 2) / 2 : M.d + 1; }
 // The calling thread's last gmhc_orbit_pass_static error (static_pass.hip).
 const char* static_last_error();
 

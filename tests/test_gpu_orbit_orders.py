@@ -1,0 +1,41 @@
+"""Gauss-Legendre orders between one point and the exact order, on and off the tile, against the
+CPU oracle at the same order.  Tolerances as in test_gpu_orbit_quadrature.py."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2609_36383_amd import workloads as W
+from test_gpu_parity import _gpu, _rel, _say
+from test_gpu_point_passes import MESH, _particles
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dim,gl", [(2, 2), (3, 2), (3, 3)])
+@pytest.mark.parametrize("num,order", [(4001, "cells"), (1500, "random"), (640, "seam")])
+def test_orders_below_the_exact_one(dim, gl, num, order):
+    G = _gpu()
+    n, length = MESH[dim]
+    seed, dt = 140 + dim, 0.3
+    gphi, An, Anp1, _ = W.random_fields(dim, n, length, seed=seed, amp=0.3)
+    Uh = (Anp1 - An) / dt
+    x, u, q = _particles(dim, num, order, seed + 1)
+    rng = np.random.default_rng(seed + 2)
+    P = rng.normal(size=(3, num)) * 0.01 * np.abs(q)[None, :]
+    vbar = rng.uniform(-0.9, 0.9, (3, num))
+    kw = dict(dim=dim, n=n, lo=(0.0,) * dim, length=length, dt=dt, gl_order=gl)
+    osim = O.OracleSim(O.make_config(**kw))
+    osim.load_particles(x, u, q)
+    osim.set_particle_state(x, P, vbar)
+    ref = osim.orbit_pass(gphi, An, Anp1, Uh, vbar, iterate=False)
+    for prec, tol in ((G.FP64, 1e-12), (G.FP32_BULK, 2e-5)):
+        sim = G.Simulation(G.make_config(**kw, precision=prec), num)
+        sim.load_particles(x, u, q)
+        sim.set_particle_state(x, P, vbar)
+        sim.set_frozen_fields(gphi, An, Anp1, Uh)
+        rep = sim.orbit_pass_frozen(iterate=False)
+        vout, Pn1, J = sim.read_pass()
+        sim.close()
+        err = (_rel(vout, ref["vout"]), _rel(Pn1, ref["Pnp1"]), _rel(J, ref["J"]))
+        _say(f"d={dim} gl={gl} np={num} {order} prec={prec}: v {err[0]:.1e} P {err[1]:.1e} J {err[2]:.1e}")
+        assert rep["failed"] == 0 and max(err) < tol
