@@ -30,6 +30,8 @@ def _load(sim, x, u, q):
     n, d = sim.np, sim.d
     if (all(t.device == sim.device and t.dtype == torch.float64 for t in (x, u, q))
             and (x.numel(), u.numel(), q.numel()) == (d * n, 3 * n, n)):
+        # the library reads the memory itself: a lazy negation is carried out first
+        x, u, q = (t.resolve_neg() for t in (x, u, q))
         x, u, q = x.reshape(d, n).contiguous(), u.reshape(3, n).contiguous(), q.reshape(n).contiguous()
         # the library's stream starts after what made the tensors; it is idle again, and the
         # tensors free, when the call returns
