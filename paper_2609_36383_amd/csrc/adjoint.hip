@@ -662,6 +662,8 @@ struct WinAcc {
     }
     return in ? r : -1;
   }
+  // The rest is for the 1D scatter.  rel of node x along the first axis:
+  __device__ __forceinline__ int rel1(int x) const { return x >= wlo[0] && x < wlo[0] + kWinX<D> ? x - wlo[0] : -1; }
   // The put of NE entries by a whole wave whose lanes all target the same window nodes
   // (every lane active; a lane without a value passes zeros): entry e has the value
   // val(e) on each lane and the window entry ent(e) (field * window nodes + node, the
@@ -687,20 +689,19 @@ struct WinAcc {
       }
     }
   }
-  // The put of a whole wave (every lane active; a lane without a value passes v = 0).
+  // The put of one value per lane at its node (every lane active; one without passes v = 0).
   // Lanes whose limbs go to the same window entry are summed across the wave first and
   // added by one lane, which takes the 64-way same-address serialization off the LDS
   // atomics; up to two such groups are taken, the rest add their own limbs.  Integer sums
   // do not depend on the grouping, so every entry ends with the same bits as when each
   // lane adds its own limbs.
-  __device__ __forceinline__ void put_wave(int f, int r, const int node[D], double v, int lane) const {
+  __device__ __forceinline__ void put_wave(int f, int node, double v, int lane) const {
+    const int r = rel1(node);
     long long H, L;
     fix_split(v, up, H, L);
     const bool c = (H | L) != 0;
     if (c && r < 0) {
-      int gi = wrapi(node[0], M->n[0]);
-      if (D > 1) gi += M->n[0] * wrapi(node[D > 1 ? 1 : 0], M->n[1]);
-      if (D > 2) gi += M->n[0] * M->n[1] * wrapi(node[D > 2 ? 2 : 0], M->n[2]);
+      const int gi = wrapi(node, M->n[0]);
       if (H) atomicAdd(g + 2 * ((int64_t)f * M->Ng + gi), (unsigned long long)H);
       if (L) atomicAdd(g + 2 * ((int64_t)f * M->Ng + gi) + 1, (unsigned long long)L);
     }
@@ -1240,41 +1241,37 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SCAT && 
       scatter_nodes<D, false>(w, rec, base, v, live, e ? D + 3 : D, lane);
     }
   } else {
-    // Every lane of the wave takes part (a lane with no particle, or no segment at a step,
+    // 1D.  Every lane of the wave takes part (a lane with no particle, or no segment at a step,
     // puts zeros), so the puts can sum across the wave.  Within a knot-split segment the
-    // stencil nodes stay the same, so each node's weights are integrated over the segment's
-    // Gauss points first (int S, int (1 - s) dS/dx_l, int s dS/dx_l) and scattered once per
+    // three nodes stay the same, so each node's weights are integrated over the segment's
+    // Gauss points first (int S, int (1 - s) dS/dx, int s dS/dx) and scattered once per
     // segment.
     SegWalk<D> sw;
     sw.init(xi0, dxi, live);
 #pragma unroll 1
-    for (int step = 0; step <= D * (kMaxCross + 1); ++step) {
+    for (int step = 0; step <= kMaxCross + 1; ++step) {
       if (__ballot(sw.live) == 0) break;
       const bool has = sw.step();
       const double sa = has ? sw.sa : 0.0, sb = has ? sw.sb : 0.0, len = sb - sa;
-      int base[D];
-      for (int l = 0; l < D; ++l) base[l] = (int)floor(xi0[l] + 0.5 * (sa + sb) * dxi[l] + 0.5);
-      constexpr int NK = kStencil<D>;
-      double I0[NK], Ia[NK][D], Ib[NK][D];
-#pragma unroll
-      for (int k = 0; k < NK; ++k) {
-        I0[k] = 0.0;
-        for (int l = 0; l < D; ++l) Ia[k][l] = Ib[k][l] = 0.0;
-      }
+      const int b0 = (int)floor(xi0[0] + 0.5 * (sa + sb) * dxi[0] + 0.5), base = b0 + sh[0];
+      double I0[3] = {0.0, 0.0, 0.0}, Ia[3] = {0.0, 0.0, 0.0}, Ib[3] = {0.0, 0.0, 0.0};
       for (int q = 0; q < a.ngl; ++q) {
-        const double s = sa + len * a.glx[q], wq = len * a.glw[q];
-        double xs[D];
-        for (int l = 0; l < D; ++l) xs[l] = xi0[l] + s * dxi[l];
+        const double s = sa + len * a.glx[q], wq = len * a.glw[q], xs = xi0[0] + s * dxi[0];
 #pragma unroll
-        for (int k = 0; k < NK; ++k) {
+        for (int k = 0; k < 3; ++k) {
           // the node's weight and derivative, evaluated at the offset itself
-          const double t = xs[0] - (double)(base[0] + k - 1), dS = s2d(t) * M.inv_h[0];
+          const double t = xs - (double)(b0 + k - 1), dS = s2d(t) * M.inv_h[0];
           I0[k] += wq * s2(t);
-          Ia[k][0] += wq * (1.0 - s) * dS;
-          Ib[k][0] += wq * s * dS;
+          Ia[k] += wq * (1.0 - s) * dS;
+          Ib[k] += wq * s * dS;
         }
       }
       sw.advance(xi0, dxi);
+      // entry e = k NV + f of node k: I0_k g_0, then the A^n and A^{n+1} integrals
+      auto value = [&](int e) -> double {
+        const int k = e / NV, f = e % NV;
+        return f == 0 ? I0[k] * g[0] : (f < 4 ? Ia[k] : Ib[k]) * g[1 + (f - 1) % 3];
+      };
       // Sorted particles: the lanes of a wave fall in a few groups that share their base
       // node, and a group whose nodes lie in the window has all its entries summed over the
       // wave at once.  Lanes left over put each entry on their own.
@@ -1283,122 +1280,44 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SCAT && 
       for (int grp = 0; grp < 8; ++grp) {
         const uint64_t pm = __ballot(pend);
         if (pm == 0) break;
-        const int lead = __ffsll((long long)pm) - 1;
-        int bl[D];
-        bool mine = pend;
-        for (int l = 0; l < D; ++l) {
-          bl[l] = __builtin_amdgcn_readlane(base[l] + sh[l], lead);
-          mine = mine && base[l] + sh[l] == bl[l];
-        }
-        bool inwin = true;
-#pragma unroll
-        for (int k = 0; k < NK; ++k) {
-          int node[D];
-          for (int l = 0; l < D; ++l) node[l] = bl[l] + k - 1;
-          inwin = inwin && w.rel(node) >= 0;
-        }
-        if (!inwin) break;
-        // entry e = k NV + f: I0_k g_f (f < D), then the A^n and A^{n+1} integrals
-        w.template put_all<NK * NV>(
-            [&](int e) -> double {
-              const int k = e / NV, f = e % NV;
-              if (!mine) return 0.0;
-              if (f < D) return I0[k] * g[f];
-              const int c = f < D + 3 ? f - D : f - D - 3;
-              double v = 0.0;
-              for (int l = 0; l < D; ++l) v += (f < D + 3 ? Ia[k][l] : Ib[k][l]) * g[D + c * D + l];
-              return v;
-            },
-            [&](int e) -> int {
-              const int k = e / NV, f = e % NV;
-              int node[D];
-              for (int l = 0; l < D; ++l) node[l] = bl[l] + k - 1;
-              return f * kWinNodes<D> + w.rel(node);
-            },
-            lane);
+        const int bl = __builtin_amdgcn_readlane(base, __ffsll((long long)pm) - 1);
+        const bool mine = pend && base == bl;
+        if (w.rel1(bl - 1) < 0 || w.rel1(bl + 1) < 0) break;
+        w.template put_all<3 * NV>([&](int e) -> double { return mine ? value(e) : 0.0; },
+                                   [&](int e) -> int { return e % NV * kWinNodes<D> + w.rel1(bl + e / NV - 1); }, lane);
         pend = pend && !mine;
       }
       if (__ballot(pend) == 0) continue;
 #pragma unroll
-      for (int k = 0; k < NK; ++k) {
-        int node[D];
-        for (int l = 0; l < D; ++l) node[l] = base[l] + k - 1 + sh[l];
-        const int r = w.rel(node);
-        for (int l = 0; l < D; ++l) w.put_wave(l, r, node, pend ? I0[k] * g[l] : 0.0, lane);
-        for (int c = 0; c < 3; ++c) {
-          double va = 0.0, vb = 0.0;
-          for (int l = 0; l < D; ++l) {
-            va += Ia[k][l] * g[D + c * D + l];
-            vb += Ib[k][l] * g[D + c * D + l];
-          }
-          w.put_wave(D + c, r, node, pend ? va : 0.0, lane);
-          w.put_wave(D + 3 + c, r, node, pend ? vb : 0.0, lane);
-        }
-      }
+      for (int e = 0; e < 3 * NV; ++e) w.put_wave(e % NV, base + e / NV - 1, pend ? value(e) : 0.0, lane);
     }
     // the endpoint interpolants A^- (at x) and A^+ (at x + dt vbar)
 #pragma unroll 1
-    for (int e = 0; e < 2; ++e) {
-      double xs[D], ge[3];
-      int b[D];
-      for (int l = 0; l < D; ++l) {
-        xs[l] = xi0[l] + (e ? dxi[l] : 0.0);
-        b[l] = (int)floor(xs[l] + 0.5);
-      }
-      for (int c = 0; c < 3; ++c) ge[c] = live ? (e ? g[4 * D + 3 + c] : g[4 * D + c]) : 0.0;
+    for (int end = 0; end < 2; ++end) {
       if (__ballot(live) == 0) break;
-      // the stencil weights per axis; entry e = 3 k + c holds S_k ge_c
-      double ax[D][3];
-      for (int l = 0; l < D; ++l)
-        for (int o = 0; o < 3; ++o) ax[l][o] = s2(xs[l] - (double)(b[l] + o - 1));
+      const double xs = xi0[0] + (end ? dxi[0] : 0.0);
+      const int b0 = (int)floor(xs + 0.5), base = b0 + sh[0], f0 = end ? 4 : 1;
+      double ge[3], S[3];
+      for (int c = 0; c < 3; ++c) ge[c] = live ? (end ? g[7 + c] : g[4 + c]) : 0.0;
+      for (int k = 0; k < 3; ++k) S[k] = s2(xs - (double)(b0 + k - 1));
       // the groups of lanes sharing their nearest node, as for the segments
       bool pend = live;
 #pragma unroll 1
       for (int grp = 0; grp < 4; ++grp) {
         const uint64_t pm = __ballot(pend);
         if (pm == 0) break;
-        const int lead = __ffsll((long long)pm) - 1;
-        int bl[D], lo[D], hi[D];
-        bool mine = pend;
-        for (int l = 0; l < D; ++l) {
-          bl[l] = __builtin_amdgcn_readlane(b[l] + sh[l], lead);
-          mine = mine && b[l] + sh[l] == bl[l];
-          lo[l] = bl[l] - 1;
-          hi[l] = bl[l] + 1;
-        }
-        if (w.rel(lo) < 0 || w.rel(hi) < 0) break;
-        w.template put_all<3 * kStencil<D>>(
-            [&](int en) -> double {
-              const int k = en / 3, c = en % 3;
-              double S = 1.0;
-              for (int l = 0; l < D; ++l) S *= ax[l][NodeWeights<D>::off(l, k)];
-              return mine ? S * ge[c] : 0.0;
-            },
-            [&](int en) -> int {
-              const int k = en / 3, c = en % 3;
-              int node[D];
-              for (int l = 0; l < D; ++l) node[l] = bl[l] + NodeWeights<D>::off(l, k) - 1;
-              return ((e ? D + 3 : D) + c) * kWinNodes<D> + w.rel(node);
-            },
-            lane);
+        const int bl = __builtin_amdgcn_readlane(base, __ffsll((long long)pm) - 1);
+        const bool mine = pend && base == bl;
+        if (w.rel1(bl - 1) < 0 || w.rel1(bl + 1) < 0) break;
+        w.template put_all<9>([&](int e) -> double { return mine ? S[e / 3] * ge[e % 3] : 0.0; },
+                              [&](int e) -> int { return (f0 + e % 3) * kWinNodes<D> + w.rel1(bl + e / 3 - 1); }, lane);
         pend = pend && !mine;
       }
       if (__ballot(pend) == 0) continue;
-#pragma unroll 1
-      for (int k = 0; k < kStencil<D>; ++k) {
-        int node[D];
-        double S = 1.0;
 #pragma unroll
-        for (int l = 0; l < D; ++l) {
-          node[l] = b[l] + NodeWeights<D>::off(l, k) - 1;
-          S *= s2(xs[l] - (double)node[l]);
-          node[l] += sh[l];
-        }
-        const int r = w.rel(node);
-        for (int c = 0; c < 3; ++c) w.put_wave((e ? D + 3 : D) + c, r, node, pend ? S * ge[c] : 0.0, lane);
-      }
+      for (int e = 0; e < 9; ++e) w.put_wave(f0 + e % 3, base + e / 3 - 1, pend ? S[e / 3] * ge[e % 3] : 0.0, lane);
     }
-    }
+  }
   __syncthreads();
   for (int k = threadIdx.x; k < NV * kWinNodes<D>; k += kBlock) {
     const unsigned long long H = sacc[2 * k], L = sacc[2 * k + 1];

@@ -352,7 +352,7 @@ int32_t run_orbit(gmhc_ctx* ctx, int iterate, double* ms) {
   if (a.rstate) HIPCK(launch_refine_reset(ctx->rstate, ctx->np, ctx->stream));
   ctx->pass_levels = a.rstate != nullptr;
   const bool timed = ctx->timed_now;
-  HIPCK(launch_orbit(a, ctx->ngl, ctx->stream, timed ? ctx->ev0 : nullptr, timed ? ctx->ev1 : nullptr));
+  HIPCK(launch_orbit(a, ctx->stream, timed ? ctx->ev0 : nullptr, timed ? ctx->ev1 : nullptr));
   const int nb = (int)((ctx->np + kOrbitBlock - 1) / kOrbitBlock);
   if (nb > 0) {
     const ReduceSet r = reduce_chunks(
@@ -925,7 +925,7 @@ int32_t enqueue_outer(gmhc_ctx* ctx, int cur, int hs, int part, const int32_t* s
     const bool timed = ctx->timed_now && (part == OUTER_ORBIT || stop != nullptr);
     OrbitArgs oa = orbit_args(ctx, 1, par);
     oa.stop = stop;
-    HIPCK(launch_orbit(oa, ctx->ngl, s, timed ? e0 : nullptr, timed ? e1 : nullptr));
+    HIPCK(launch_orbit(oa, s, timed ? e0 : nullptr, timed ? e1 : nullptr));
     ctx->vin_first = false;  // later passes of the step start from their predecessor's v_out
   }
   if (part == OUTER_ALL || part == OUTER_POST || part == OUTER_TAIL) {

@@ -108,7 +108,7 @@ struct OrbitArgs {
 // separate marker packets on the stream); with no particles both are recorded at once.
 // With refinement (a.rstate set) the refinement pass follows the main pass in the same
 // call, and the events span both.
-hipError_t launch_orbit(const OrbitArgs& a, int ngl, hipStream_t s, hipEvent_t e0 = nullptr,
+hipError_t launch_orbit(const OrbitArgs& a, hipStream_t s, hipEvent_t e0 = nullptr,
                         hipEvent_t e1 = nullptr);
 // Every particle back to the full step (refinement level 0), at the start of a step.
 hipError_t launch_refine_reset(int32_t* rstate, int64_t np, hipStream_t s);

@@ -169,15 +169,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 3 && SH
 #pragma unroll 1
   for (int64_t w0 = b0; w0 < b1; w0 += kPointWindow) {
     const int wn = (int)(b1 - w0 < kPointWindow ? b1 - w0 : kPointWindow);
-    Batches bt;
-    bt.begin();
     __syncthreads();
-    bt.next<kPointWindow>(wn, list, [&](int r) {
+    const int nb = list_batches<kPointWindow>(wn, list, [&](int r) {
       if (a.keys) return a.keys[w0 + r];
       double f[D];
       return locate(w0 + r, f);
     });
-    if (kPointBatch * bt.nb > wn) {  // scattered particles: one per lane
+    if (kPointBatch * nb > wn) {  // scattered particles: one per lane
 #pragma unroll 1
       for (int r = lane; r < wn; r += 64) {
         const int64_t i = a.perm ? a.perm[w0 + r] : w0 + r;
@@ -200,11 +198,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 3 && SH
       }
       continue;
     }
-    const int rounds = (bt.nb + 3) >> 2;
+    const int rounds = (nb + 3) >> 2;
 #pragma unroll 1
     for (int t = 0; t < rounds; ++t) {
       const int b = row * rounds + t;
-      const bool on = b < bt.nb;
+      const bool on = b < nb;
       const int lo = on ? list[b] : 0;
       const bool live = on && rl < list[on ? b + 1 : 0] - lo;
       const int64_t r = w0 + (live ? lo + rl : 0);
@@ -228,7 +226,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 3 && SH
           const double* base = a.A[0] + (rl < 3 ? rl : 0) * M.Ng;
 #pragma unroll
           for (int p = 0; p < NP; ++p) cf[p] = base[cell_node<D>(M, home, p % N - off, (p / N) % N - off, p / (N * N) - off)];
-          all_axes<D, SH, false>(cf);
+          all_to_powers<D, SH>(cf);
           tag = home;
         }
         double Ah[3] = {0.0, 0.0, 0.0};

@@ -18,23 +18,17 @@
 namespace gmhc {
 namespace {
 
-// acc += (lane L of the row's c) * w: an FP64 or FP32 multiply-add whose first factor is read
+// acc += (lane L of the row's c) * w: an FP64 multiply-add whose first factor is read
 // from lane L of each row of sixteen lanes (DPP row broadcast), at the full rate and without
 // LDS.  Every lane of the wave must be active.  The wait states cover a VALU write of c just
 // before (two are needed ahead of a DPP read) and a transcendental result in w.
-#define GMHC_FMAC(SUF, ACC, C, W, L) \
-  "v_fmac_" SUF "_dpp " ACC ", " C ", " W " row_newbcast:" L " row_mask:0xf bank_mask:0xf\n\t"
-#define GMHC_ROW_OPS(T, SUF)                                                                        \
-  template <int L>                                                                                  \
-  __device__ __forceinline__ void row_fma3(T& a0, T& a1, T& a2, T c, T w) {                         \
-    asm("s_nop 1\n\t" GMHC_FMAC(SUF, "%0", "%3", "%4", "%5") GMHC_FMAC(SUF, "%1", "%3", "%4", "%6") \
-            GMHC_FMAC(SUF, "%2", "%3", "%4", "%7")                                                  \
-        : "+v"(a0), "+v"(a1), "+v"(a2)                                                              \
-        : "v"(c), "v"(w), "n"(L), "n"(L + 1), "n"(L + 2));                                          \
-  }
-GMHC_ROW_OPS(double, "f64")
-GMHC_ROW_OPS(float, "f32")
-#undef GMHC_ROW_OPS
+#define GMHC_FMAC(ACC, L) "v_fmac_f64_dpp " ACC ", %3, %4 row_newbcast:" L " row_mask:0xf bank_mask:0xf\n\t"
+template <int L>
+__device__ __forceinline__ void row_fma3(double& a0, double& a1, double& a2, double c, double w) {
+  asm("s_nop 1\n\t" GMHC_FMAC("%0", "%5") GMHC_FMAC("%1", "%6") GMHC_FMAC("%2", "%7")
+      : "+v"(a0), "+v"(a1), "+v"(a2)
+      : "v"(c), "v"(w), "n"(L), "n"(L + 1), "n"(L + 2));
+}
 #undef GMHC_FMAC
 
 template <int D, int SH>
@@ -95,58 +89,48 @@ __device__ __forceinline__ void to_nodes(T* v, int st) {
     v[2 * st] = t + h;
   }
 }
-template <int D, int SH, bool NODES, class T>
-__device__ __forceinline__ void all_axes(T* v) {
+template <int D, int SH, class T>
+__device__ __forceinline__ void all_to_powers(T* v) {
   constexpr int N = SH + 1, NP = powers<D, SH>();
 #pragma unroll
   for (int l = 0, st = 1; l < D; ++l, st *= N)
 #pragma unroll
     for (int p = 0; p < NP; ++p)
-      if ((p / st) % N == 0) {
-        if constexpr (NODES)
-          to_nodes<SH>(v + p, st);
-        else
-          to_powers<SH>(v + p, st);
-      }
+      if ((p / st) % N == 0) to_powers<SH>(v + p, st);
 }
 
 // ---- batches of one cell
 //
-// A wave cuts a window of consecutive particles into batches: runs of one cell cut every
-// sixteen particles, so that each batch fits a row of lanes.
-struct Batches {
-  int nb, c0, carry, run;  // batches listed; next particle, its predecessor's cell and run
-  __device__ __forceinline__ void begin() {
-    nb = c0 = run = 0;
-    carry = INT_MIN;
+// A wave cuts a window of wn consecutive particles, at most MAX, into batches: runs of one cell cut
+// every sixteen particles, so that each batch fits a row of lanes.  list[b] is the first particle of
+// batch b, list[(the number returned)] the end; cell(r) is the cell of particle r of the window (any
+// r < wn).  All 64 lanes call it.
+template <int MAX, class Cell>
+__device__ __forceinline__ int list_batches(int wn, uint16_t* list, Cell&& cell) {
+  static_assert(MAX <= 65535, "list holds 16-bit indices");
+  const int lane = threadIdx.x & 63;
+  const uint64_t below = (1ull << lane) - 1ull;
+  int nb = 0, carry = INT_MIN, run = 0;  // the last particle's cell and the start of its run
+  for (int c0 = 0; c0 < wn; c0 += 64) {
+    const int r = c0 + lane;
+    const bool in = r < wn;
+    const int g = cell(in ? r : wn - 1);
+    int prev = __shfl_up(g, 1);
+    if (lane == 0) prev = carry;
+    const uint64_t starts = __ballot(in && g != prev);
+    const uint64_t upto = starts & (below | (1ull << lane));
+    const int first = upto ? c0 + 63 - __builtin_clzll(upto) : run;
+    const bool bs = in && ((r - first) & 15) == 0;
+    const uint64_t bm = __ballot(bs);
+    if (bs) list[nb + __popcll(bm & below)] = (uint16_t)r;
+    nb += __popcll(bm);
+    carry = __builtin_amdgcn_readlane(g, 63);
+    if (starts) run = c0 + 63 - __builtin_clzll(starts);
   }
-  // Lists the next batches of the window of wn particles (whole groups of 64 while CAP
-  // batches have room): list[b] is the first particle of batch b, list[nb] the end.
-  // cell(r): the cell of particle r of the window (any r < wn).  All 64 lanes call it.
-  template <int CAP, class Cell>
-  __device__ __forceinline__ void next(int wn, uint16_t* list, Cell&& cell) {
-    const int lane = threadIdx.x & 63, first0 = c0;
-    for (nb = 0; c0 < wn && nb + 64 <= CAP; c0 += 64) {
-      const int r = c0 + lane;
-      const bool in = r < wn;
-      const int g = cell(in ? r : wn - 1);
-      int prev = __shfl_up(g, 1);
-      if (lane == 0) prev = carry;
-      const uint64_t starts = __ballot(in && g != prev);
-      const uint64_t below = (1ull << lane) - 1ull;
-      const uint64_t upto = starts & (below | (1ull << lane));
-      const int first = upto ? c0 + 63 - __builtin_clzll(upto) : run;
-      const bool bs = in && (((r - first) & 15) == 0 || r == first0);
-      const uint64_t bm = __ballot(bs);
-      if (bs) list[nb + __popcll(bm & below)] = (uint16_t)r;
-      nb += __popcll(bm);
-      carry = __builtin_amdgcn_readlane(g, 63);
-      if (starts) run = c0 + 63 - __builtin_clzll(starts);
-    }
-    if (lane == 0) list[nb] = (uint16_t)(c0 < wn ? c0 : wn);
-    __syncthreads();
-  }
-};
+  if (lane == 0) list[nb] = (uint16_t)wn;
+  __syncthreads();
+  return nb;
+}
 
 // Base cell of a position (linear index) and the offset from its base node.
 template <int D, int SH>
@@ -203,11 +187,11 @@ __device__ __forceinline__ void row_sums(RowBuffer& b, double* t, Val&& val) {
   }
 }
 
-// The row's totals t (value 16 c + rl on lane rl; K components of (SH+1)^DD moments each)
+// The row's totals t (value 16 c + rl on lane rl; K components of (SH+1)^D moments each)
 // into node values, axis by axis, left in the row's part tb of LDS; t is cleared.
-template <int K, int DD, int SH>
+template <int K, int D, int SH>
 __device__ __forceinline__ void row_to_nodes(double* tb, double* t, int rl) {
-  constexpr int N = SH + 1, NM = DD == 0 ? 1 : powers<DD == 0 ? 1 : DD, SH>(), NV = K * NM, NL = NV / N;
+  constexpr int N = SH + 1, NV = K * powers<D, SH>(), NL = NV / N;
   __syncthreads();
 #pragma unroll
   for (int c = 0; c < (NV + 15) / 16; ++c) {
@@ -215,7 +199,7 @@ __device__ __forceinline__ void row_to_nodes(double* tb, double* t, int rl) {
     t[c] = 0.0;
   }
 #pragma unroll
-  for (int l = 0, st = 1; l < DD; ++l, st *= N) {
+  for (int l = 0, st = 1; l < D; ++l, st *= N) {
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < (NL + 15) / 16; ++u) {

@@ -152,7 +152,7 @@ int32_t gmhc_orbit_pass_static(const gmhc_config* cfg, int64_t n, const double* 
   a.J = Jfx;
   a.partials = partials;
   a.pstride = kStaticBlocks;
-  if ((st = ck(launch_orbit(a, ngl, s), "orbit pass"))) return st;
+  if ((st = ck(launch_orbit(a, s), "orbit pass"))) return st;
   const int nb = (int)((n + kOrbitBlock - 1) / kOrbitBlock);
   if (nb > 0) {
     const ReduceSet r =
