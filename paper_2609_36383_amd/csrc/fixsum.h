@@ -55,6 +55,12 @@ __device__ __forceinline__ void fix_add(unsigned long long* acc, int64_t i, doub
   if (L) atomicAdd(acc + 2 * i + 1, (unsigned long long)L);
 }
 
+// The pair with its low limb in [0, 2^K): the same for every way the same sum was added.
+__device__ __forceinline__ void fix_normalize(long long& H, long long& L) {
+  H += L >> kFixK;
+  L &= (1ll << kFixK) - 1;
+}
+
 __device__ __forceinline__ double fix_value(const unsigned long long* acc, int64_t i, double hi, double lo) {
   return (double)(long long)acc[2 * i] * hi + (double)(long long)acc[2 * i + 1] * lo;
 }

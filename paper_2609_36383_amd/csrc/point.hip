@@ -5,19 +5,20 @@
 // What bounded the thread-per-particle forms: the deposit added 4 (SH+1)^d values per
 // particle through 64-bit atomics, and neighbouring particles hit the same nodes; the gathers
 // read 3 (SH+1)^d scattered mesh values per particle.  Here a row of sixteen lanes takes a
-// batch of particles of one cell: the deposit is summed over the batch, and over the row's
-// following batches of the same cell, as moments before a node is touched, and the gather
-// reads the cell's three polynomials once per row and broadcasts their coefficients.  At
+// batch of particles of one cell: the deposit's node values are summed over the batch, and over
+// the row's following batches of the same cell, before a node is touched (exactly, so the mesh sums
+// do not depend on the particles' order), and the gather reads the cell's three polynomials once per
+// row and broadcasts their coefficients.  At
 // initialization the particles may be in any order, so where it pays (point_order_pays) they are
 // taken through their stable order by cell (an index sort; the storage order stays).  Elsewhere
 // the storage order serves, and a window whose particles are too scattered (fewer than four per
 // batch on average) takes one particle per lane.
 //
 // Measured at 8,388,608 particles on 64^3 (32 per cell, in grid-cell order): the deposit 76.2
-// to 0.80 ms (the index sort adds 0.3 ms), the canonical momenta 1.74 to 0.59 ms, the kinetic
-// energy 1.71 to 0.75 ms; the traffic none of them can do without takes 0.1 ms.  At 67,108,864
-// particles on 512^2 the deposit took 222 ms.  Left: instruction issue (LDS sums of 108
-// moments per batch, gathers of 27 coefficients per cell).
+// to 0.85 ms (0.81 with rounded sums of the cell's moments; the index sort adds 0.3 ms), the
+// canonical momenta 1.74 to 0.61 ms, the kinetic energy 1.71 to 0.54 ms; the traffic none of them can
+// do without takes 0.1 ms.  At 67,108,864 particles on 512^2 the deposit took 222 ms.  Left:
+// instruction issue (exact LDS sums of 108 values per batch, gathers of 27 coefficients per cell).
 #include <math.h>
 
 #include <algorithm>
@@ -32,6 +33,7 @@ namespace {
 constexpr int kPointWindow = 256;  // particles per listing of batches, at most
 constexpr int kPointBatch = 4;     // particles per batch of a window, on average and at least, for the row path
 constexpr int kPointFill = 2048;   // workgroups that fill the chip (two waves per SIMD)
+static_assert(kExactSumMax % kPointWindow == 0, "a row's sums are cleared between windows");
 
 struct PointArgs {
   Mesh M;
@@ -52,32 +54,50 @@ struct PointArgs {
 
 enum PointMode { kDeposit = 0, kCanonical = 1, kKinetic = 2 };
 
+// Weights of the nodes of one axis at the offset f.
+template <int SH>
+__device__ __forceinline__ void axis_weights(double f, double* w) {
+  if constexpr (SH == 1) {
+    w[0] = 1.0 - f;
+    w[1] = f;
+  } else {
+    const double a = 0.5 - f, b = 0.5 + f;
+    w[0] = 0.5 * a * a;
+    w[1] = fma(-f, f, 0.75);
+    w[2] = 0.5 * b * b;
+  }
+}
+
 // The stencil of one particle read or written node by node.
 template <int D, int SH, class F>
 __device__ __forceinline__ void each_node(const Mesh& M, int cell, const double* f, F&& fn) {
   constexpr int N = SH + 1, NP = powers<D, SH>(), off = SH == 2 ? 1 : 0;
   double w[D][N];
 #pragma unroll
-  for (int l = 0; l < D; ++l) {
-    if constexpr (SH == 1) {
-      w[l][0] = 1.0 - f[l];
-      w[l][1] = f[l];
-    } else {
-      const double a = 0.5 - f[l], b = 0.5 + f[l];
-      w[l][0] = 0.5 * a * a;
-      w[l][1] = 0.75 - f[l] * f[l];
-      w[l][2] = 0.5 * b * b;
-    }
-  }
+  for (int l = 0; l < D; ++l) axis_weights<SH>(f[l], w[l]);
   // a row of nodes along x at a time, so that its reads are in flight together
 #pragma unroll 1
   for (int r = 0; r < NP / N; ++r) {
     const int j = r % N, k = r / N;
-    double s = 1.0;
-    if constexpr (D > 1) s *= j == 0 ? w[1][0] : (j == 1 ? w[1][1] : w[1][N - 1]);
-    if constexpr (D > 2) s *= k == 0 ? w[2][0] : (k == 1 ? w[2][1] : w[2][N - 1]);
+    const double wy = D < 2 ? 1.0 : (j == 0 ? w[D > 1][0] : (j == 1 ? w[D > 1][1] : w[D > 1][N - 1]));
+    const double wz = D < 3 ? 1.0 : (k == 0 ? w[D - 1][0] : (k == 1 ? w[D - 1][1] : w[D - 1][N - 1]));
 #pragma unroll
-    for (int i = 0; i < N; ++i) fn(cell_node<D>(M, cell, i - off, j - off, k - off), s * w[0][i]);
+    for (int i = 0; i < N; ++i) fn(cell_node<D>(M, cell, i - off, j - off, k - off), w[0][i] * wy * wz);
+  }
+}
+
+// The same weights at once: the same products in the same order, so a particle adds the same
+// values in a row and by itself.
+template <int D, int SH>
+__device__ __forceinline__ void node_weights(const double* f, double* s) {
+  constexpr int N = SH + 1, NP = powers<D, SH>();
+  double w[D][N];
+#pragma unroll
+  for (int l = 0; l < D; ++l) axis_weights<SH>(f[l], w[l]);
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const double wy = D < 2 ? 1.0 : w[D > 1][p / N % N], wz = D < 3 ? 1.0 : w[D - 1][p / (N * N)];
+    s[p] = w[0][p % N] * wy * wz;
   }
 }
 
@@ -94,10 +114,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 3 && SH
   double part[3] = {0.0, 0.0, 0.0};  // kinetic energy, sum |q| (v_y^2 + v_z^2), sum |q|
   double cf[NP];
   int tag = -1;
-  double tot[NC];
+  const ExactScale fx(M.fx);
+  ExactSum tot[NC];
   int jt = -1;
 #pragma unroll
-  for (int c = 0; c < NC; ++c) tot[c] = 0.0;
+  for (int c = 0; c < NC; ++c) tot[c].clear(fx);
 #pragma unroll
   for (int p = 0; p < NP; ++p) cf[p] = 0.0;
 
@@ -148,27 +169,27 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 3 && SH
   auto flush = [&]() __attribute__((always_inline)) {
     int r = rl;
     asm volatile("" : "+v"(r));  // keeps the lane's indices out of the registers of the main loop
-    double* tb = &buf.v[0][0] + row * (4 * NP);
-    row_to_nodes<4, D, SH>(tb, tot, r);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const int o = 16 * c + r;
-      const double v = o < 4 * NP ? tb[o] : 0.0;
-      if (v != 0.0 && jt >= 0) {
+      if (o < 4 * NP && jt >= 0) {
         const int k = o / NP, nd = o - k * NP;
         const int g = cell_node<D>(M, jt, nd % N - off, (nd / N) % N - off, nd / (N * N) - off);
         if (k == 0)
-          fix_add(a.rho, g, v, M.fx.up);
+          tot[c].add_to(fx, a.rho, g);
         else
-          fix_add(a.J, (int64_t)(k - 1) * M.Ng + g, v, M.fx.up);
+          tot[c].add_to(fx, a.J, (int64_t)(k - 1) * M.Ng + g);
       }
+      tot[c].clear(fx);
     }
-    __syncthreads();
   };
 
 #pragma unroll 1
   for (int64_t w0 = b0; w0 < b1; w0 += kPointWindow) {
     const int wn = (int)(b1 - w0 < kPointWindow ? b1 - w0 : kPointWindow);
+    if constexpr (MODE == kDeposit) {  // the most values an exact sum takes
+      if ((w0 - b0) % kExactSumMax == 0 && w0 > b0 && __ballot(jt >= 0) != 0) flush();
+    }
     __syncthreads();
     const int nb = list_batches<kPointWindow>(wn, list, [&](int r) {
       if (a.keys) return a.keys[w0 + r];
@@ -185,8 +206,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 3 && SH
           double coef[4];
           velocity(i, coef);
           each_node<D, SH>(M, cell, f, [&](int g, double s) {
-            fix_add(a.rho, g, coef[0] * s, M.fx.up);
-            for (int c = 0; c < 3; ++c) fix_add(a.J, c * M.Ng + g, coef[1 + c] * s, M.fx.up);
+            fix_add(a.rho, g, rounded(coef[0] * s), M.fx.up);
+            for (int c = 0; c < 3; ++c) fix_add(a.J, c * M.Ng + g, rounded(coef[1 + c] * s), M.fx.up);
           });
         } else {
           double Ah[3] = {0.0, 0.0, 0.0};
@@ -210,7 +231,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 3 && SH
       double f[D], m[NP];
       const int cell = locate(i, f);
       int home = row_first(live ? cell : -1);
-      monomials<D, SH>(f, 1.0, m);
+      if constexpr (MODE == kDeposit)
+        node_weights<D, SH>(f, m);
+      else
+        monomials<D, SH>(f, 1.0, m);
       if constexpr (MODE == kDeposit) {
         double coef[4] = {0.0, 0.0, 0.0, 0.0};
         if (live) velocity(i, coef);
@@ -219,7 +243,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 3 && SH
           if (__ballot(jt >= 0) != 0) flush();
           jt = home;
         }
-        row_sums<4 * NP>(buf, tot, [&](int o) { return coef[o / NP] * m[o % NP]; });
+        row_sums<4 * NP>(buf, tot, fx, [&](int o) { return coef[o / NP] * m[o % NP]; });
       } else {
         if (home < 0) home = max(tag, 0);
         if (__ballot(tag != home) != 0) {  // lane c of the row holds A_c of the cell

@@ -4,8 +4,8 @@
 // Inside one cell a field of the spline of degree SH is a polynomial sum_p F_p X^i/i! Y^j/j!
 // Z^k/k!, p = i + (SH+1) (j + (SH+1) k), in the offset from the cell's base node (the nearest
 // node for SH = 2, the node below for SH = 1).  A gather is a contraction of the coefficients
-// F_p with the monomials at the particle; a deposit sums the particles' monomials over the
-// cell and turns the sums into node values once (the transpose).
+// F_p with the monomials at the particle.  A deposit sums the particles' node values over the
+// cell before a node is touched, as exact integers.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -13,6 +13,7 @@
 #include <stdint.h>
 
 #include "cell.h"
+#include "fixsum.h"
 #include "gmhc_internal.h"
 
 namespace gmhc {
@@ -74,19 +75,6 @@ __device__ __forceinline__ void to_powers(T* v, int st) {
     v[0] = b + T(0.125) * s;
     v[st] = T(0.5) * (c - a);
     v[2 * st] = s;
-  }
-}
-// The transpose: moments of the cell's monomials along one axis into node weights.
-template <int SH, class T>
-__device__ __forceinline__ void to_nodes(T* v, int st) {
-  if constexpr (SH == 1) {
-    v[0] = v[0] - v[st];
-  } else {
-    const T a = v[0], b = v[st], c = v[2 * st];
-    const T t = T(0.125) * a + c, h = T(0.5) * b;
-    v[0] = t - h;
-    v[st] = T(0.75) * a - (c + c);
-    v[2 * st] = t + h;
   }
 }
 template <int D, int SH, class T>
@@ -163,9 +151,48 @@ struct RowBuffer {
   double v[16][66];
 };
 
-// t[c] += the sum over the row of value 16 c + (lane of the row), for the NV values val(o).
+// Exact sums of FP64 values rounded to the fixed-point resolution q = 2^-s (fixsum.h), in two FP64
+// numbers.  hi, offset by 3 2^91 q = 3 B, keeps every partial sum in one binade, so that adding v
+// rounds it to a multiple of 2^40 q and the part left over, at most 2^39 q, is exact; that part is
+// rounded to a multiple of q (to nearest, ties to even, as fix_add rounds v) and summed in lo, exactly
+// for up to 2^13 values.  What reaches a node is therefore what its values would add one by one,
+// whatever the order and the rows: particles that are mirror images leave mirror images.
+constexpr int kExactSumMax = 1 << 13;
+struct ExactScale {
+  double hi0, lo0, hi_inv, lo_inv;
+  __device__ __forceinline__ explicit ExactScale(const FixScale& f)
+      : hi0(f.lo * (3.0 * 0x1p91)), lo0(f.lo * (1.5 * 0x1p52)), hi_inv(f.up * 0x1p-10), lo_inv(f.up * 0x1p30) {}
+};
+static_assert(kFixK == 30, "the limbs of ExactSum::add_to and the scale");
+struct ExactSum {
+  double hi, lo;
+  __device__ __forceinline__ void clear(const ExactScale& x) {
+    hi = x.hi0;
+    lo = 0.0;
+  }
+  __device__ __forceinline__ void add(const ExactScale& x, double v) {
+    const double h = hi + v;
+    const double r = v - (h - hi);
+    hi = h;
+    lo += (r + x.lo0) - x.lo0;
+  }
+  __device__ __forceinline__ void add_to(const ExactScale& x, unsigned long long* acc, int64_t i) const {
+    const long long h = (long long)((hi - x.hi0) * x.hi_inv), l = (long long)(lo * x.lo_inv);
+    const long long H = (h << 10) + (l >> kFixK), L = l & ((1ll << kFixK) - 1);
+    if (H) atomicAdd(acc + 2 * i, (unsigned long long)H);
+    if (L) atomicAdd(acc + 2 * i + 1, (unsigned long long)L);
+  }
+};
+
+// v as rounded to FP64: its product is not contracted into what follows.
+__device__ __forceinline__ double rounded(double v) {
+  asm("" : "+v"(v));
+  return v;
+}
+
+// t[c] += the row's values 16 c + (lane of the row), for the NV values val(o).
 template <int NV, class Val>
-__device__ __forceinline__ void row_sums(RowBuffer& b, double* t, Val&& val) {
+__device__ __forceinline__ void row_sums(RowBuffer& b, ExactSum* t, const ExactScale& x, Val&& val) {
   const int lane = threadIdx.x & 63, rl = lane & 15;
 #pragma unroll
   for (int c = 0; c < (NV + 15) / 16; ++c) {
@@ -173,41 +200,19 @@ __device__ __forceinline__ void row_sums(RowBuffer& b, double* t, Val&& val) {
 #pragma unroll
     for (int o = 16 * c; o < 16 * c + 16 && o < NV; ++o) b.v[o - 16 * c][lane] = val(o);
     __syncthreads();
-    if (16 * c + rl < NV) {
-      const double2* v = reinterpret_cast<const double2*>(&b.v[rl][lane & 48]);
-      double2 r = v[0];
+    // every lane sums a row of the buffer; those past the NV values are not used
+    const double2* v = reinterpret_cast<const double2*>(&b.v[rl][lane & 48]);
+    double2 u[8];
 #pragma unroll
-      for (int l = 1; l < 8; ++l) {
-        const double2 u = v[l];
-        r.x += u.x;
-        r.y += u.y;
-      }
-      t[c] += r.x + r.y;
+    for (int l = 0; l < 8; ++l) u[l] = v[l];
+#pragma unroll
+    for (int l = 0; l < 8; ++l) {
+      t[c].add(x, u[l].x);
+      t[c].add(x, u[l].y);
     }
+    // in place: sums left for later would hold every chunk's values in registers
+    asm volatile("" : "+v"(t[c].hi), "+v"(t[c].lo));
   }
-}
-
-// The row's totals t (value 16 c + rl on lane rl; K components of (SH+1)^D moments each)
-// into node values, axis by axis, left in the row's part tb of LDS; t is cleared.
-template <int K, int D, int SH>
-__device__ __forceinline__ void row_to_nodes(double* tb, double* t, int rl) {
-  constexpr int N = SH + 1, NV = K * powers<D, SH>(), NL = NV / N;
-  __syncthreads();
-#pragma unroll
-  for (int c = 0; c < (NV + 15) / 16; ++c) {
-    if (16 * c + rl < NV) tb[16 * c + rl] = t[c];
-    t[c] = 0.0;
-  }
-#pragma unroll
-  for (int l = 0, st = 1; l < D; ++l, st *= N) {
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < (NL + 15) / 16; ++u) {
-      const int ln = rl + 16 * u;
-      if (ln < NL) to_nodes<SH>(tb + (ln / st) * st * N + ln % st, st);
-    }
-  }
-  __syncthreads();
 }
 
 }  // namespace

@@ -635,7 +635,10 @@ __global__ void k_axpy2(double* y, const double* x, double2* yc, const double2* 
 __global__ __launch_bounds__(kBlock) void k_fix_to_double(const unsigned long long* acc, double* out, int64_t n,
                                                           FixScale fx) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = fix_value(acc, i, fx.hi, fx.lo);
+  if (i >= n) return;
+  long long H = (long long)acc[2 * i], L = (long long)acc[2 * i + 1];
+  fix_normalize(H, L);
+  out[i] = (double)H * fx.hi + (double)L * fx.lo;
 }
 
 // Sum of |q| (bound of the charge and current sums per node): one value per block in
