@@ -184,12 +184,6 @@ struct ExactSum {
   }
 };
 
-// v as rounded to FP64: its product is not contracted into what follows.
-__device__ __forceinline__ double rounded(double v) {
-  asm("" : "+v"(v));
-  return v;
-}
-
 // t[c] += the row's values 16 c + (lane of the row), for the NV values val(o).
 template <int NV, class Val>
 __device__ __forceinline__ void row_sums(RowBuffer& b, ExactSum* t, const ExactScale& x, Val&& val) {
