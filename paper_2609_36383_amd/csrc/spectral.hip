@@ -187,9 +187,9 @@ __device__ __forceinline__ int brev_n(int k, int logN) {
   return logN > 0 ? (int)(__brev((unsigned)k) >> (32 - logN)) : 0;
 }
 
-// Where line element i of a workgroup's LDS block sits: the low four bits are exchanged with
-// the next four, so that the bit-reversed load and store, whose neighbouring lanes are
-// multiples of sixteen elements (all 64 banks) apart, reach every bank.
+// Where line element i of a workgroup's LDS block sits: its low four bits XOR the next four, so
+// that the bit-reversed load and store, whose neighbouring lanes are multiples of sixteen
+// elements (all 64 banks) apart, reach every bank.
 __device__ __forceinline__ int fft_at(int i) { return i ^ ((i >> 4) & 15); }
 
 // LR butterfly stages of `count` lines' elements (lines of N = 2^logN) in one trip through
