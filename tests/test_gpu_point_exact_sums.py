@@ -33,3 +33,36 @@ def test_fields_do_not_depend_on_the_order(dim, shape, num):
         sim.close()
         ref = ref or got
         assert all(np.array_equal(a, b) for a, b in zip(got, ref))
+
+
+def test_more_values_than_one_exact_sum_takes():
+    """Above 8,192 particles per workgroup (67,108,864 in all) a row's sums are put away in between:
+    here all particles sit in two cells, so that rows go on with one cell throughout."""
+    import ctypes as C
+
+    import torch
+    G = _gpu()
+    num, dev, f64 = 8192 * 8192 + 300007, "cuda:0", torch.float64
+    n, length = MESH[1]
+    g = torch.Generator(device=dev).manual_seed(190)
+    h = length[0] / n[0]
+    x = (31.5 + torch.rand(num, generator=g, device=dev, dtype=f64)) * h
+    x[num // 2:] += h
+    u = torch.rand(3, num, generator=g, device=dev, dtype=f64) - 0.5
+    q = -(0.5 + torch.rand(num, generator=g, device=dev, dtype=f64)) / num
+    # without the projector, which takes the Nyquist mode out of the fields read
+    sim = G.Simulation(G.make_config(dim=1, n=n, lo=(0.0,), length=length, dt=0.05, project_nyquist=0), num, device=dev)
+    ref = None
+    for _ in range(2):
+        sim.stream.wait_stream(torch.cuda.current_stream())
+        ptr = [C.c_void_p(t.data_ptr()) for t in (x, u, q)]
+        assert sim.lib.gmhc_load_particles(sim.h, *ptr, G.DEVICE) == G.OK
+        sim.initialize()
+        got = [sim.read_field(f) for f in ("rho", "J")]
+        ref = ref or got
+        x, u, q = x.flip(0), u.flip(1).contiguous(), q.flip(0)
+    sim.close()
+    assert all(np.array_equal(a, b) for a, b in zip(got, ref))
+    # the charge of the two cells' nodes, against the sum over the particles
+    total = float(got[0].sum() - got[0][0] * n[0]) * h
+    assert abs(total / float(q.sum()) - 1.0) < 1e-12
