@@ -236,9 +236,10 @@ def run_case(args, w, fp32, parts, tol_of_fp32=None):
     d = w["dim"]
     ng = int(np.prod(w["n"]))
     seg_mean = segs / max(evals, 1)  # measured knot-split segments per evaluation
-    # the kernel's quadrature: closed form (-1), points of the least exact order, or the run's points (0)
+    # the kernel's quadrature: closed form (-1), points of the least exact order (3D FP32), or the
+    # run's points (0)
     exact = d + 1 if sh == 2 else (d + 2) // 2
-    quad = 0 if ngl < exact else (exact if fp32 else -1)
+    quad = 0 if ngl < exact else (exact if fp32 and d == 3 else -1)
     # flops of the timed launches (evaluations per launch of the timed steps)
     flops_launch = (timed_evals / max(timed_launches, 1)) * flops_per_eval(d, seg_mean, ngl, sh)
     bytes_launch = npart * bytes_per_particle(d, 4 if fp32 else 8) + ng * bytes_per_node(d)
