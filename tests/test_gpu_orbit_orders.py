@@ -39,3 +39,35 @@ def test_orders_below_the_exact_one(dim, gl, num, order):
         err = (_rel(vout, ref["vout"]), _rel(Pn1, ref["Pnp1"]), _rel(J, ref["J"]))
         _say(f"d={dim} gl={gl} np={num} {order} prec={prec}: v {err[0]:.1e} P {err[1]:.1e} J {err[2]:.1e}")
         assert rep["failed"] == 0 and max(err) < tol
+
+
+# 2D FP32 reads the mesh with the points of the least exact order, whatever higher one is asked for
+@pytest.mark.parametrize("shape", [2, 1])
+def test_fp32_orders_from_the_exact_one_on_off_the_tile(shape):
+    G = _gpu()
+    n, length = MESH[2]
+    num, dt = 1500, 0.3
+    gphi, An, Anp1, _ = W.random_fields(2, n, length, seed=146, amp=0.3)
+    Uh = (Anp1 - An) / dt
+    x, u, q = _particles(2, num, "random", 147)
+    rng = np.random.default_rng(148)
+    P = rng.normal(size=(3, num)) * 0.01 * np.abs(q)[None, :]
+    vbar = rng.uniform(-0.9, 0.9, (3, num))
+    kw = dict(dim=2, n=n, lo=(0.0, 0.0), length=length, dt=dt, shape_order=shape)
+    osim = O.OracleSim(O.make_config(**kw, gl_order=8))
+    osim.load_particles(x, u, q)
+    osim.set_particle_state(x, P, vbar)
+    ref = osim.orbit_pass(gphi, An, Anp1, Uh, vbar, iterate=False)
+    out = []
+    for gl in (0, 8):
+        sim = G.Simulation(G.make_config(**kw, gl_order=gl, precision=G.FP32_BULK), num)
+        sim.load_particles(x, u, q)
+        sim.set_particle_state(x, P, vbar)
+        sim.set_frozen_fields(gphi, An, Anp1, Uh)
+        rep = sim.orbit_pass_frozen(iterate=False)
+        out.append(sim.read_pass())
+        sim.close()
+        err = [_rel(a, ref[k]) for a, k in zip(out[-1], ("vout", "Pnp1", "J"))]
+        _say(f"S{shape} gl={gl}: v {err[0]:.1e} P {err[1]:.1e} J {err[2]:.1e}")
+        assert rep["failed"] == 0 and max(err) < 2e-5
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
